@@ -54,6 +54,8 @@
 
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "switchsd_internal.h"
 
 namespace switchsd {
@@ -130,6 +132,19 @@ union Shared {
     PickShared pick;
     DrawShared draw;
 };
+// The sum launches at T > 0: a row's weight table (weight_table), then the
+// shared memory of whatever closes the row.
+constexpr int kTabHalf = 2560;  // entries per sign
+// Chunks per work-group from which the sum launch uses the table: making it
+// takes 20 weights per lane, a chunk 32 logits per lane.  With one chunk
+// (8 x 11 rows of 128256) the table made the launch 12.4 -> 15.2 us, with three
+// (32 x 8 rows) 23.1 -> 20.6 us.
+constexpr int kTableChunks = 3;
+union SumShared {
+    Shared s;
+    float tab[2 * kTabHalf];
+};
+static_assert(sizeof(SumShared) == 20480, "eight work-groups per CU");
 
 // Timeline build only (compiled with SWITCHSD_TIMELINE, never in the product
 // library): per work-group stamps of the 100 MHz real-time clock, slot
@@ -2090,7 +2105,7 @@ __device__ __forceinline__ unsigned long long scaled_target(unsigned long long u
 // contiguous range in index order.
 __device__ __forceinline__ void load_chunk_w(u32x4 (&v)[kUnroll], const u32x4 *vp, int qc0,
                                              int nq) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = (threadIdx.x >> 6) & (kWaves - 1), lane = threadIdx.x & 63;
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
         const int q = qc0 + wave * (kUnroll * 64) + u * 64 + lane;
@@ -2098,19 +2113,93 @@ __device__ __forceinline__ void load_chunk_w(u32x4 (&v)[kUnroll], const u32x4 *v
     }
 }
 
+// Table of a row's weights.  A weight depends on the logit's 16 bits alone
+// (m and c are the row's), so the sum launches compute each bit pattern's
+// weight once per work-group and row, into LDS, and look it up per logit: 5.5
+// VALU operations and one 4-byte LDS read instead of the 17 operations of
+// samp_weight.  The values are samp_weight's own, so the sums are the same
+// integers.  The table holds the kTabHalf - 1 magnitudes (20 binades less one
+// pattern) below the first power of two beyond which a weight is zero, both
+// signs interleaved.  Entry kTabHalf - 1 stands for every larger magnitude
+// (values below m - 41 / c, -inf and NaN: weight 0; none lies above m) and
+// entry 0 for every smaller one, whose weight the table does not have: a NaN
+// there makes its vector's sum a NaN, and the wave computes that vector
+// directly.
+//
+// The table pays where few logits are that small: bottom = 2^-20 of the
+// power of two above |m| + 41 / c; with |m| at 4.5 standard deviations and
+// |m| + 41 / c = 128 |m|, 45% of the 512-logit vectors of a wave would hold one
+// and cost about what the direct form does, so beyond that ratio the row is
+// computed directly.
+__device__ __forceinline__ float table_limit(float m, float c) {
+    return __builtin_fabsf(m) + 41.0f / c;
+}
+__device__ __forceinline__ bool table_pays(float m, float c) {
+    return __builtin_fabsf(m) * 128.0f >= table_limit(m, c);
+}
+// The magnitude bits entry 0 stands for (and all below them).
+__device__ __forceinline__ uint32_t table_base(float m, float c) {
+    const int e = (int)(__float_as_uint(table_limit(m, c)) >> 23) + 1;
+    return (uint32_t)clampi(e, 20, 255) * 128u - (uint32_t)(kTabHalf - 1);
+}
+// Every thread of the work-group calls this; barriers around it are the
+// caller's.
+template <int kBlock>
+__device__ __forceinline__ void weight_table(float *tab, uint32_t base, float m, float c) {
+    static_assert(2 * kTabHalf % kBlock == 0, "whole rounds");
+#pragma unroll 1
+    for (int i = threadIdx.x; i < 2 * kTabHalf; i += kBlock) {
+        const uint32_t a = (uint32_t)i >> 1;
+        const float l = __uint_as_float(((base + a) << 16) | ((uint32_t)(i & 1) << 31));
+        const float w = samp_weight(l, m, c);
+        tab[i] = a == kTabHalf - 1 ? 0.0f : (a == 0 ? __builtin_nanf("") : w);
+    }
+}
+// As vec_weight, from the table; a NaN where it lacks an element.
+__device__ __forceinline__ double vec_lookup(const u32x4 &v, const float *tab, uint32_t base) {
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+    const u16x2 lo = {(uint16_t)base, (uint16_t)base};
+    const u16x2 hi = {(uint16_t)(kTabHalf - 1), (uint16_t)(kTabHalf - 1)};
+    const char *t = reinterpret_cast<const char *>(tab);
+    float w[8];
+#pragma unroll
+    for (int w4 = 0; w4 < 4; ++w4) {
+        const uint32_t x = v[w4];
+        u16x2 d = __builtin_bit_cast(u16x2, x & 0x7FFF7FFFu);
+        d = __builtin_elementwise_min(__builtin_elementwise_sub_sat(d, lo), hi);
+        // byte offsets 8 entry + 4 sign, below 2^16
+        const uint32_t o = (__builtin_bit_cast(uint32_t, d) << 3) | ((x >> 13) & 0x00040004u);
+        w[2 * w4] = *reinterpret_cast<const float *>(t + (o & 0xFFFFu));
+        w[2 * w4 + 1] = *reinterpret_cast<const float *>(t + (o >> 16));
+    }
+    return (((double)w[0] + (double)w[1]) + ((double)w[2] + (double)w[3])) +
+           (((double)w[4] + (double)w[5]) + ((double)w[6] + (double)w[7]));
+}
+
 // Weight sums of chunk c (16 KB) of a row, one per wave (its contiguous 256
 // vectors), stored at cs[c * kWaves + wave] (plus `mark`: 1 where a poller
 // tells a written sum from an empty slot); the entries of a row in index
-// order are chunk by chunk, wave by wave.
+// order are chunk by chunk, wave by wave.  kTable: the weights come from the
+// row's table.
+template <bool kTable>
 __device__ __forceinline__ void store_block_sums(const u32x4 (&A)[kUnroll], int c, int nq, float m,
-                                                 float samp_c, unsigned long long *cs,
+                                                 float samp_c, const float *tab, uint32_t base,
+                                                 unsigned long long *cs,
                                                  unsigned long long mark) {
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int wave = (threadIdx.x >> 6) & (kWaves - 1), lane = threadIdx.x & 63;
     const int q0 = c * kChunkVecs + wave * (kUnroll * 64) + lane;
     double w = 0.0;
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u)
-        w += q0 + u * 64 < nq ? vec_weight(A[u], m, samp_c) : 0.0;
+    for (int u = 0; u < kUnroll; ++u) {
+        if (kTable) {
+            double x = vec_lookup(A[u], tab, base);
+            if (__any(x != x))
+                x = vec_weight(A[u], m, samp_c);
+            w += q0 + u * 64 < nq ? x : 0.0;
+        } else {
+            w += q0 + u * 64 < nq ? vec_weight(A[u], m, samp_c) : 0.0;
+        }
+    }
     w = wave_sum_f64(w);
     if (lane == 0)
         __hip_atomic_store(&cs[c * kWaves + wave], (unsigned long long)w + mark,
@@ -2585,9 +2674,10 @@ __device__ void draw_poller(const StepParams &p, int b, int r, int dn_raw, unsig
 // in the grid) does the same for the q rows that have a drafted child.  With
 // the polled draw, the work-group of each row's first segment then draws the
 // row's token (draw_poller); else the last one to arrive does (row_done).
-template <bool kCommit>
+template <bool kCommit, bool kTable>
 __global__ __launch_bounds__(kThreads) void k_sample_sums(StepParams p) {
-    __shared__ Shared sh;
+    __shared__ SumShared ss;
+    Shared &sh = ss.s;
     // segment-major, as the argmax role of the step kernel
     const int nrows = p.B * p.R;
     int idx = blockIdx.x;
@@ -2629,13 +2719,25 @@ __global__ __launch_bounds__(kThreads) void k_sample_sums(StepParams p) {
     unsigned long long *cs =
         (qrow ? p.qcsum : p.csum) + ((int64_t)b * p.R + r) * p.cpr * kWaves;
     const unsigned long long mark = p.draw_poll ? 1ull : 0ull;
-    for (int c = c0; active && c < c1; ++c) {
-        if (c + 1 < c1)
-            load_chunk_w(Bv, vp, (c + 1) * kChunkVecs, nq);
-        store_block_sums(A, c, nq, m, p.samp_c, cs, mark);
+    auto sums = [&](auto table, uint32_t base) {
+        for (int c = c0; c < c1; ++c) {
+            if (c + 1 < c1)
+                load_chunk_w(Bv, vp, (c + 1) * kChunkVecs, nq);
+            store_block_sums<decltype(table)::value>(A, c, nq, m, p.samp_c, ss.tab, base, cs,
+                                                     mark);
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u)
-            A[u] = Bv[u];
+            for (int u = 0; u < kUnroll; ++u)
+                A[u] = Bv[u];
+        }
+    };
+    if (kTable && active && table_pays(m, p.samp_c)) {
+        const uint32_t base = table_base(m, p.samp_c);
+        weight_table<kThreads>(ss.tab, base, m, p.samp_c);
+        __syncthreads();
+        sums(std::true_type{}, base);
+        __syncthreads();  // the table's space is the draw's next
+    } else if (active) {
+        sums(std::false_type{}, 0u);
     }
     if (p.draw_poll) {
         if (s == 0)
@@ -2659,7 +2761,8 @@ __global__ __launch_bounds__(kThreads) void k_sample_sums(StepParams p) {
 template <bool kCommit>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void
 k_sample_sums_stream(StepParams p) {
-    __shared__ Shared sh;
+    __shared__ SumShared ss;
+    Shared &sh = ss.s;
     const int lane = threadIdx.x & 63;
     constexpr int Q = kListMaxB / 64;
     const int cpr = p.cpr;
@@ -2712,6 +2815,8 @@ k_sample_sums_stream(StepParams p) {
     load_chunk_w(A, row_vecs(b, r), c * kChunkVecs, nq);
     unsigned long long key = ld_u64(&p.ws.keys[(int64_t)b * p.ws.key_stride + r]);
     uint32_t done_r = 0;  // units of row (b, r) streamed here
+    uint32_t base = 0;    // of the row's weight table
+    bool tabled = false;
     for (int u = u0; u < u1; ++u) {
         int nb = b, nr = r, nc = c + 1, ndn = dnb;
         if (nc == cpr) {
@@ -2738,9 +2843,19 @@ k_sample_sums_stream(StepParams p) {
         }
         float m = 0.0f;
         const bool active = key_max(key, m);
-        if (active)
-            store_block_sums(A, c, nq, m, p.samp_c,
-                             p.csum + ((int64_t)b * p.R + r) * cpr * kWaves, 0ull);
+        unsigned long long *cs = p.csum + ((int64_t)b * p.R + r) * cpr * kWaves;
+        if (done_r == 0) {  // first chunk of this row's piece (the same in every thread)
+            tabled = active && table_pays(m, p.samp_c);
+            if (tabled) {
+                base = table_base(m, p.samp_c);
+                weight_table<kThreads>(ss.tab, base, m, p.samp_c);
+                __syncthreads();
+            }
+        }
+        if (tabled)
+            store_block_sums<true>(A, c, nq, m, p.samp_c, ss.tab, base, cs, 0ull);
+        else if (active)
+            store_block_sums<false>(A, c, nq, m, p.samp_c, ss.tab, base, cs, 0ull);
         ++done_r;
         if (c == cpr - 1 || u + 1 == u1) {  // end of this row's piece
             row_done<kCommit>(p, b, r, dnb, done_r, (uint32_t)cpr, false, sh);
@@ -2755,6 +2870,308 @@ k_sample_sums_stream(StepParams p) {
         for (int q = 0; q < kUnroll; ++q)
             A[q] = Bv[q];
     }
+}
+
+// Draw at T > 0 with whole rows in registers: one work-group of 16 waves per
+// compute unit takes a drafted row at a time (rows blockIdx.x, + grid, ... of
+// the batch's drafted rows r < dn[b]), holds it in registers (kVecs 16-byte
+// vectors per lane; wave w the vectors [64 kVecs w, 64 kVecs (w + 1))), and
+// finds the maximum, the weight sums and the drawn token from one read of the
+// row.  As a vector's weights are summed, its registers take the same vector
+// of the work-group's next row, so the reads go on under the sums.  The only
+// hand-off between work-groups is the sequence's arrival count: the last of
+// its rows runs the accept epilogue.  Nothing waits for another work-group.
+constexpr int kRowThreads = 1024;
+constexpr int kRowWaves = kRowThreads / 64;
+constexpr int kRowMaxVecs = kRowVecs;  // per lane: V <= 1024 * 8 * kRowMaxVecs
+struct RowShared {
+    float tab[2 * kTabHalf];
+    unsigned long long ent[kRowWaves * kRowMaxVecs / kUnroll];  // weight sums per 256 vectors
+    int32_t first[kListMaxB + 1];  // drafted rows before each sequence
+    int32_t closed[kListMaxB];     // sequences whose last row was drawn here
+    uint32_t mi[kRowWaves];        // the waves' maxima (16-bit patterns, biased)
+    float mf[kRowWaves];           // the same as floats where the patterns do not tell
+    uint32_t mn[kRowWaves];        // lowest index (rows without a finite maximum)
+    Shared s;                      // the accept epilogue's (wave 0)
+};
+
+template <int kVecs, bool kCommit>
+__global__ __launch_bounds__(kRowThreads)
+__attribute__((amdgpu_waves_per_eu(kVecs <= kRowVecsTwo ? 8 : 4))) void k_row_draw(StepParams p) {
+    __shared__ RowShared sh;
+    constexpr int G = kVecs / kUnroll;  // entries of 256 vectors per wave
+    constexpr int E = kRowWaves * G;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    if (wave == 0) {  // prefix sums of the drafted rows
+        int32_t dnq[kListMaxB / 64];
+#pragma unroll
+        for (int q = 0; q < kListMaxB / 64; ++q) {
+            const int b = lane + 64 * q;
+            dnq[q] = ld_i32(&p.dn[b < p.B ? b : p.B - 1]);
+        }
+        int carry = 0;
+#pragma unroll
+        for (int q = 0; q < kListMaxB / 64; ++q) {
+            const int b = lane + 64 * q;
+            const int cnt = b < p.B ? clampi(dnq[q], 1, p.R) : 0;
+            int inc = cnt;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int y = __shfl_up(inc, o);
+                if (lane >= o)
+                    inc += y;
+            }
+            if (b <= p.B)
+                sh.first[b] = carry + inc - cnt;
+            carry += __shfl(inc, 63);
+        }
+        if (lane == 0)
+            sh.first[p.B] = carry;
+    }
+    __syncthreads();
+    const int U = sh.first[p.B];
+    // sequence and row of the j-th drafted row (every sequence has at least one)
+    auto locate = [&](int j, int &b, int &r, int &dnb) {
+        int n = 0;
+#pragma unroll
+        for (int q = 0; q < kListMaxB / 64; ++q) {
+            const int i = lane + 64 * q;
+            n += __popcll(__ballot(i < p.B && sh.first[i < p.B ? i : p.B] <= j));
+        }
+        b = __builtin_amdgcn_readfirstlane(n - 1);
+        const int f = __builtin_amdgcn_readfirstlane(sh.first[b]);
+        r = j - f;
+        dnb = __builtin_amdgcn_readfirstlane(sh.first[b + 1]) - f;
+    };
+    int j = blockIdx.x;
+    if (j >= U)
+        return;
+    int n_closed = 0;
+    const int nq = p.V >> 3;
+    const int qw = wave * (kVecs * 64) + lane;
+    int b, r, dnb;
+    locate(j, b, r, dnb);
+    auto row_vecs = [&](int bb, int rr) {
+        return reinterpret_cast<const u32x4 *>(p.logits + ((int64_t)bb * p.R + rr) * p.V);
+    };
+    const u32x4 *vp = row_vecs(b, r);
+    unsigned long long uni = p.uniforms[(int64_t)b * p.R + r];
+    u32x4 A[kVecs];
+    // buffer loads: one offset register for all of a lane's vectors (a clamped
+    // index per vector kept 14 of them in scratch memory, whose reads then
+    // waited behind the row's)
+    const int voff = qw * 16;
+    auto load = [&](const u32x4 *rv, int u) {
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<u32x4 *>(rv), 0, p.V * 2, 0x00027000);
+        return __builtin_bit_cast(u32x4,
+                                  __builtin_amdgcn_raw_buffer_load_b128(rs, voff, u * 1024, 2));
+    };
+    const bool tail = (wave + 1) * kVecs * 64 > nq;  // some vectors lie past the row's end
+#pragma unroll
+    for (int u = 0; u < kVecs; ++u)
+        A[u] = load(vp, u);
+    for (;;) {
+        // vectors past the row's end become negative NaN, which no maximum
+        // takes and whose weight is 0
+        if (tail) {
+#pragma unroll
+            for (int u = 0; u < kVecs; ++u)
+                if (qw + u * 64 >= nq)
+                    A[u] = u32x4{~0u, ~0u, ~0u, ~0u};
+        }
+        // the row's maximum: packed 16-bit maxima of the bit patterns, which
+        // order values >= +0
+        float m;
+        {
+            s16x2 M = as_s16x2(0x80008000u);
+#pragma unroll
+            for (int u = 0; u < kVecs; ++u)
+#pragma unroll
+                for (int w4 = 0; w4 < 4; ++w4)
+                    M = __builtin_elementwise_max(M, as_s16x2(A[u][w4]));
+            const int mm = M[0] > M[1] ? M[0] : M[1];
+            const uint32_t wm = wave_max_u32((uint32_t)(mm + 0x8000));
+            if (lane == 0)
+                sh.mi[wave] = wm;
+            __syncthreads();
+            const int k = (int)wave_max_u32(sh.mi[lane & (kRowWaves - 1)]) - 0x8000;
+            m = __uint_as_float((uint32_t)k << 16);
+            if (k < 0 || k > 0x7F80) {  // no element >= +0, or a positive NaN: as floats
+                float f = __builtin_nanf("");
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    u32x4 c[kUnroll];
+#pragma unroll
+                    for (int u = 0; u < kUnroll; ++u)
+                        c[u] = A[g * kUnroll + u];
+                    f = fmax_first(f, chunk_max(c));
+                }
+                // (a NaN lane has no number; NaN for the row only if every lane is)
+                const bool any = __any(f == f);
+                f = wave_max_f32(f == f ? f : -__builtin_inff());
+                if (lane == 0)
+                    sh.mf[wave] = any ? f : __builtin_nanf("");
+                __syncthreads();
+                const float y = sh.mf[lane & (kRowWaves - 1)];
+                const bool some = __any(y == y);
+                m = wave_max_f32(y == y ? y : -__builtin_inff());
+                m = some ? m : __builtin_nanf("");
+            }
+        }
+        const bool finite = __builtin_isfinite(m);
+        const int jn = j + (int)gridDim.x;
+        const bool more = jn < U;
+        int bn = b, rn = r, dn_n = dnb;
+        if (more)
+            locate(jn, bn, rn, dn_n);
+        const u32x4 *vn = row_vecs(bn, rn);
+        const unsigned long long uni_n = p.uniforms[(int64_t)bn * p.R + rn];
+        uint32_t base = 0;
+        bool direct = true;
+        if (finite) {
+            direct = !table_pays(m, p.samp_c);
+            if (!direct) {
+                base = table_base(m, p.samp_c);
+                weight_table<kRowThreads>(sh.tab, base, m, p.samp_c);
+            }
+            __syncthreads();
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            double w = 0.0;
+#pragma unroll
+            for (int v = 0; v < kUnroll; ++v) {
+                const int u = g * kUnroll + v;
+                if (finite) {
+                    double x = __builtin_nan("");
+                    if (!direct)
+                        x = vec_lookup(A[u], sh.tab, base);
+                    if (__any(x != x))
+                        x = vec_weight(A[u], m, p.samp_c);
+                    w += x;
+                }
+                if (more)
+                    A[u] = load(vn, u);
+            }
+            if (finite) {
+                w = wave_sum_f64(w);
+                if (lane == 0)
+                    sh.ent[wave * G + g] = (unsigned long long)w;
+            }
+        }
+        if (!finite) {
+            // one-hot at the lowest index of the maximum (0 when all are NaN)
+            uint32_t lo = kNoIdx;
+            for (int q = tid; q < nq; q += kRowThreads) {
+                const u32x4 v = vp[q];
+                for (int e = 7; e >= 0; --e) {
+                    const uint32_t x = v[e >> 1];
+                    if (((e & 1) ? hi_f(x) : lo_f(x)) == m && 8u * q + e < lo)
+                        lo = 8u * q + e;
+                }
+            }
+            lo = wave_min_u32(lo);
+            if (lane == 0)
+                sh.mn[wave] = lo;
+        }
+        __syncthreads();
+        if (wave == 0) {
+            uint32_t y = 0;
+            if (finite) {
+                // the entry holding the target: two per lane, in index order
+                const unsigned long long e0 = 2 * lane < E ? sh.ent[2 * lane < E ? 2 * lane : 0] : 0;
+                const unsigned long long e1 =
+                    2 * lane + 1 < E ? sh.ent[2 * lane + 1 < E ? 2 * lane + 1 : 0] : 0;
+                const unsigned long long inc = wave_scan_u64(e0 + e1);
+                unsigned long long tg = scaled_target(uni, readlane_u64(inc, 63));
+                // (the entry, block and vector exist, the target being below
+                // the total; the clamps only keep every index in range)
+                int l = __ffsll((long long)__ballot(inc > tg)) - 1;
+                l = l < 0 ? 0 : l;
+                tg -= readlane_u64(inc - e0 - e1, l);
+                const unsigned long long f0 = readlane_u64(e0, l);
+                int ent = 2 * l;
+                if (tg >= f0) {
+                    tg -= f0;
+                    ent = 2 * l + 1 < E ? 2 * l + 1 : 2 * l;
+                }
+                // its blocks of 64 vectors, read again together (the next row
+                // fills the registers meanwhile), up to the target's
+                u32x4 v[kUnroll];
+                const int qe = ent * (kUnroll * 64) + lane;
+#pragma unroll
+                for (int u = 0; u < kUnroll; ++u) {
+                    const int q = qe + u * 64;
+                    v[u] = vp[q < nq ? q : nq - 1];
+                }
+                unsigned long long w = 0, iv = 0;
+                u32x4 x = v[0];
+                int us = -1;
+#pragma unroll
+                for (int u = 0; u < kUnroll; ++u) {
+                    if (us < 0) {  // uniform
+                        double d = __builtin_nan("");
+                        if (!direct)
+                            d = vec_lookup(v[u], sh.tab, base);
+                        if (__any(d != d))
+                            d = vec_weight(v[u], m, p.samp_c);
+                        w = qe + u * 64 < nq ? (unsigned long long)d : 0ull;
+                        iv = wave_scan_u64(w);
+                        const unsigned long long tot = readlane_u64(iv, 63);
+                        if (tg < tot || u == kUnroll - 1) {
+                            us = u;
+                            x = v[u];
+                        } else {
+                            tg -= tot;
+                        }
+                    }
+                }
+                int ls = __ffsll((long long)__ballot(iv > tg)) - 1;
+                ls = __builtin_amdgcn_readfirstlane(ls < 0 ? 0 : ls);
+                tg -= readlane_u64(iv - w, ls);
+                // the vector's 8 weights in lanes 0..7, their inclusive prefix
+                uint32_t xj = 0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const uint32_t xk = (uint32_t)__builtin_amdgcn_readlane((int)x[k], ls);
+                    xj = ((lane >> 1) & 3) == k ? xk : xj;
+                }
+                unsigned long long ew = 0ull;
+                if (lane < 8)
+                    ew = (unsigned long long)samp_weight((lane & 1) ? hi_f(xj) : lo_f(xj), m,
+                                                         p.samp_c);
+                ew = wave_scan_u64<3>(ew);
+                int e = __ffsll((long long)__ballot(lane < 8 && ew > tg)) - 1;
+                e = e < 0 ? 7 : e;
+                y = (uint32_t)(ent * (kUnroll * 64) + us * 64 + ls) * 8u + (uint32_t)e;
+            } else {
+                const uint32_t lo = wave_min_u32(sh.mn[lane & (kRowWaves - 1)]);
+                y = lo == kNoIdx ? 0u : lo;
+            }
+            if (lane == 0)
+                st_u64(&p.ws.keys[(int64_t)b * p.ws.key_stride + r],
+                       (1ull << 32) | (unsigned long long)(0xFFFFFFFFu - y));
+            if (arrive(&p.ws.tk_all[b * kLineU32], (uint32_t)dnb)) {
+                if (lane == 0)
+                    sh.closed[n_closed] = b;
+                ++n_closed;
+            }
+        }
+        if (!more)
+            break;
+        j = jn;
+        b = bn;
+        r = rn;
+        dnb = dn_n;
+        vp = vn;
+        uni = uni_n;
+    }
+    // the sequences this work-group's rows were the last of (after the loop:
+    // the epilogue would share the row's registers)
+    if (wave == 0)
+        for (int i = 0; i < n_closed; ++i)
+            final_epilogue<kCommit>(p, __builtin_amdgcn_readfirstlane(sh.closed[i]), sh.s);
 }
 
 // Residual weight max(0, P_j Zq - Q_j Zp) of element j, and P_j.
@@ -3587,10 +4004,40 @@ int launch_sample_sums_kernel(const StepParams &p, int64_t grid, hipStream_t str
         hipLaunchKernelGGL((k_sample_sums_stream<true>), g, dim3(kThreads), 0, stream, p);
     else if (p.list_mode)
         hipLaunchKernelGGL((k_sample_sums_stream<false>), g, dim3(kThreads), 0, stream, p);
+    else if (p.seg_chunks >= kTableChunks)
+        if (p.commit)
+            hipLaunchKernelGGL((k_sample_sums<true, true>), g, dim3(kThreads), 0, stream, p);
+        else
+            hipLaunchKernelGGL((k_sample_sums<false, true>), g, dim3(kThreads), 0, stream, p);
     else if (p.commit)
-        hipLaunchKernelGGL((k_sample_sums<true>), g, dim3(kThreads), 0, stream, p);
+        hipLaunchKernelGGL((k_sample_sums<true, false>), g, dim3(kThreads), 0, stream, p);
     else
-        hipLaunchKernelGGL((k_sample_sums<false>), g, dim3(kThreads), 0, stream, p);
+        hipLaunchKernelGGL((k_sample_sums<false, false>), g, dim3(kThreads), 0, stream, p);
+    return hipGetLastError() == hipSuccess ? SWITCHSD_OK : SWITCHSD_EHIP;
+}
+
+template <int kVecs>
+static void launch_row_draw_vecs(const StepParams &p, unsigned grid, hipStream_t stream) {
+    if (p.commit)
+        hipLaunchKernelGGL((k_row_draw<kVecs, true>), dim3(grid), dim3(kRowThreads), 0, stream, p);
+    else
+        hipLaunchKernelGGL((k_row_draw<kVecs, false>), dim3(grid), dim3(kRowThreads), 0, stream,
+                           p);
+}
+
+int launch_row_draw_kernel(const StepParams &p, int64_t grid, hipStream_t stream) {
+    const int vecs = (p.V / 8 + kRowThreads - 1) / kRowThreads;
+    const unsigned g = (unsigned)grid;
+    if (vecs > 16)
+        launch_row_draw_vecs<20>(p, g, stream);
+    else if (vecs > 12)
+        launch_row_draw_vecs<16>(p, g, stream);
+    else if (vecs > 8)
+        launch_row_draw_vecs<12>(p, g, stream);
+    else if (vecs > kRowVecsTwo)
+        launch_row_draw_vecs<8>(p, g, stream);
+    else
+        launch_row_draw_vecs<4>(p, g, stream);
     return hipGetLastError() == hipSuccess ? SWITCHSD_OK : SWITCHSD_EHIP;
 }
 
