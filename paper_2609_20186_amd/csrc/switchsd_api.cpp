@@ -423,6 +423,30 @@ bool draw_polled(const StepParams &p, const SampleArgs *sa, int cus) {
     return !sa->qlogits && p.R <= 64 && p.ws.skey_stride > 0 && (int64_t)p.B * p.R <= cus;
 }
 
+// Work-groups of the row draw that fit the device together.
+int64_t row_slots(int32_t V, int cus) {
+    return ((int64_t)V / 8 + 1023) / 1024 <= kRowVecsTwo ? 2 * (int64_t)cus : cus;
+}
+
+// The draw with whole rows in registers, which reads the drafted rows once:
+// one-hot drafts, rows of at most 1024 * 8 * kRowVecs logits, and rows enough
+// for one and a half rounds of its work-groups.  Each takes a row at a time,
+// about 17 us for 128256 logits, after a front launch of 7 us, so with fewer
+// rows a second round would be nearly empty: 256 rows (32 x 8) measured 34 us
+// against 34 us for the maxima and sum launches, 6432 rows (32 x 201, 3344
+// drafted) 239 us against 365 us.
+bool row_draw(int32_t B, int32_t R, int32_t V, const SampleArgs *sa, int cus) {
+    return !sa->qlogits && B <= kListMaxB && V <= 1024 * 8 * kRowVecs &&
+           2 * (int64_t)B * R >= 3 * row_slots(V, cus);
+}
+
+int row_draw_launch(StepParams p, const SampleArgs *sa, int cus, hipStream_t stream) {
+    sample_carve(p, sa);
+    p.tl = nullptr;
+    const int64_t rows = (int64_t)p.B * p.R, slots = row_slots(p.V, cus);
+    return launch_row_draw_kernel(p, rows < slots ? rows : slots, stream);
+}
+
 // The row maxima launch before a draw: with the polled draw, it also zeroes
 // the sum slots (csum_clear), so the sample workspace needs no initialization.
 int prepare_draw(StepParams &p, const SampleArgs *sa) {
@@ -600,8 +624,15 @@ int verify_launch(const uint16_t *logits, int32_t B, int32_t R, int32_t V, const
     }
     p.exp_all = (uint32_t)(R * p.segs);
     p.spin_cap = 1 << 22;  // the bound of each poll (see switchsd_workspace_status)
-    if (sa && (rc = prepare_draw(p, sa)))
-        return rc;
+    if (sa) {
+        int cus = 0;
+        if ((rc = cu_count(&cus)))
+            return rc;
+        if (row_draw(B, R, V, sa, cus))
+            return row_draw_launch(p, sa, cus, stream);
+        if ((rc = prepare_draw(p, sa)))
+            return rc;
+    }
     if ((rc = launch_step_kernel(p, grid, stream)) || !sa)
         return rc;
     return sample_finish(p, sa, speculate, stream);
@@ -764,6 +795,8 @@ int switchsd_step(const switchsd_step_args *a, void *workspace, size_t workspace
     int mode = a->mode;
     if (mode == SWITCHSD_MODE_AUTO)  // short drafts that may use every row: one launch
         mode = cn >= R && R <= 64 ? SWITCHSD_MODE_FUSED : SWITCHSD_MODE_SPLIT;
+    if (mode == SWITCHSD_MODE_FUSED && sampled && row_draw(B, R, V, &sa, cus))
+        mode = SWITCHSD_MODE_SPLIT;  // the draw needs no row maxima beforehand
     if (mode == SWITCHSD_MODE_FUSED) {
         // the accept epilogue polls at most kMaxPollSlots segment results
         const int64_t cap = kMaxPollSlots / R < kMaxSegs ? kMaxPollSlots / R : kMaxSegs;

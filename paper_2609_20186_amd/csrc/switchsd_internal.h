@@ -46,6 +46,12 @@ enum : int32_t {
 // four registers per lane).
 constexpr int kListMaxB = 256;
 
+// The draw at T > 0 with whole rows in registers (one 1024-thread work-group
+// per row): 16-byte vectors per lane, at most.
+constexpr int kRowVecs = 20;
+// Up to this many, two of its work-groups fit a compute unit.
+constexpr int kRowVecsTwo = 4;
+
 struct Workspace {
     uint32_t *tk_front;        // [B] x 256 B: arrivals of the scan/probe work-groups
     uint32_t *tk_all;          // [B] x 256 B: arrivals of every work-group of a sequence
@@ -182,6 +188,7 @@ int launch_commit_kernel(const StepParams &p, hipStream_t stream);
 int launch_label_kernels(const StepParams &p, int32_t n, uint8_t *labels, int32_t tsize,
                          void *table, hipStream_t stream);
 int launch_sample_sums_kernel(const StepParams &p, int64_t grid, hipStream_t stream);
+int launch_row_draw_kernel(const StepParams &p, int64_t grid, hipStream_t stream);
 int launch_spec_residual_kernel(const StepParams &p, int64_t grid, hipStream_t stream);
 int launch_status_kernel(int32_t *mslot, int32_t B, int32_t *out, hipStream_t stream);
 int launch_tree_mask_kernel(const int32_t *dpar, const int32_t *dn, int32_t B, int32_t R,
