@@ -134,23 +134,37 @@ _DT = {"i32": (torch.int32,), "f32": (torch.float32,),
        "u32": (torch.int32, torch.uint32), "u64": (torch.int64, torch.uint64)}
 
 
+_Tensor = torch.Tensor
+
+
 def _ptr(t, kind, name, optional=False):
+    # the accepted case first: a stage call checks up to eleven tensors
+    if isinstance(t, _Tensor) and t.is_cuda and t.dtype in _DT[kind] and t.is_contiguous():
+        return t.data_ptr()
     if t is None:
         if optional:
             return None
         raise ValueError(f"{name} is required")
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
+    if not isinstance(t, _Tensor) or not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
     if t.dtype not in _DT[kind]:
         raise ValueError(f"{name} has dtype {t.dtype}, expected {_DT[kind]}")
-    if not t.is_contiguous():
-        raise ValueError(f"{name} must be contiguous")
-    return t.data_ptr()
+    raise ValueError(f"{name} must be contiguous")
+
+
+# The current stream's handle without a Stream object around it, where torch
+# offers that (six stage calls with both: 50 -> 37 us).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+_initialized = torch.cuda.is_initialized
 
 
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None or _device is None or not _initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
 
 
 def _check(fn, rc):
