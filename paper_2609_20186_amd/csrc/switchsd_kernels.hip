@@ -46,8 +46,8 @@
 //
 // Further kernels: k_verify_poll (the greedy verify launch with polling),
 // k_verify_stream (verification of long drafts over a fixed grid),
-// k_sample_sums / k_sample_sums_stream and k_spec_residual (verification at
-// sampling temperature T > 0), k_select and k_commit (stage entry points),
+// k_sample_sums / k_sample_sums_stream, k_row_draw and k_spec_residual
+// (verification at sampling temperature T > 0), k_select and k_commit (stage entry points),
 // k_tree_mask (the verification mask), k_label_insert / k_label_write /
 // k_label_clear (copy-mode labels for probe training).
 #include <hip/hip_runtime.h>
@@ -2115,16 +2115,20 @@ __device__ __forceinline__ void load_chunk_w(u32x4 (&v)[kUnroll], const u32x4 *v
 
 // Table of a row's weights.  A weight depends on the logit's 16 bits alone
 // (m and c are the row's), so the sum launches compute each bit pattern's
-// weight once per work-group and row, into LDS, and look it up per logit: 5.5
-// VALU operations and one 4-byte LDS read instead of the 17 operations of
-// samp_weight.  The values are samp_weight's own, so the sums are the same
-// integers.  The table holds the kTabHalf - 1 magnitudes (20 binades less one
-// pattern) below the first power of two beyond which a weight is zero, both
-// signs interleaved.  Entry kTabHalf - 1 stands for every larger magnitude
-// (values below m - 41 / c, -inf and NaN: weight 0; none lies above m) and
-// entry 0 for every smaller one, whose weight the table does not have: a NaN
-// there makes its vector's sum a NaN, and the wave computes that vector
-// directly.
+// weight once per work-group and row, into LDS, and look it up per logit: 6.4
+// VALU operations and one 4-byte LDS read (about 6.5 cycles per wave and
+// compute unit at random entries) instead of the 17 operations of samp_weight,
+// which bounded the launches.  The values are samp_weight's own, so the sums
+// are the same integers.  Measured per launch at T = 0.7: 32 x 8 rows of 128256
+// 23.1 -> 20.6 us, the same with q 34.8 -> 29.5 us, 3344 rows streamed 241 ->
+// 205 us.  One table per 1024-thread work-group instead (four chunks at once)
+// took 25.0 us for the 32 x 8 rows.
+// The table holds the kTabHalf - 2 magnitudes (20 binades less two patterns)
+// below the first power of two beyond which a weight is zero, both signs
+// interleaved.  Entry kTabHalf - 1 stands for every larger magnitude (values
+// below m - 41 / c, -inf and NaN: weight 0; none lies above m) and entry 0 for
+// every smaller one, whose weight the table does not have: a NaN there makes
+// its vector's sum a NaN, and the wave computes that vector directly.
 //
 // The table pays where few logits are that small: bottom = 2^-20 of the
 // power of two above |m| + 41 / c; with |m| at 4.5 standard deviations and
@@ -2881,6 +2885,12 @@ k_sample_sums_stream(StepParams p) {
 // of the work-group's next row, so the reads go on under the sums.  The only
 // hand-off between work-groups is the sequence's arrival count: the last of
 // its rows runs the accept epilogue.  Nothing waits for another work-group.
+// Bound by a row's chain: its reads (about 12 us of 17 for 128256 logits with
+// every compute unit reading), the table before the sums and the draw after
+// them, under which only the next row's reads go on.  3344 drafted rows at
+// T = 0.7: 206-226 us, against 133 us for the maxima and 205 us for the sums
+// in two streamed launches; a step with ten candidates per sequence (32) 368 ->
+// 219 us.
 constexpr int kRowThreads = 1024;
 constexpr int kRowWaves = kRowThreads / 64;
 constexpr int kRowMaxVecs = kRowVecs;  // per lane: V <= 1024 * 8 * kRowMaxVecs
