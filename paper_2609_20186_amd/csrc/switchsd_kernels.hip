@@ -2969,13 +2969,20 @@ __attribute__((amdgpu_waves_per_eu(kVecs <= kRowVecsTwo ? 8 : 4))) void k_row_dr
     u32x4 A[kVecs];
     // buffer loads: one offset register for all of a lane's vectors (a clamped
     // index per vector kept 14 of them in scratch memory, whose reads then
-    // waited behind the row's)
+    // waited behind the row's).  Vectors past the row's end must read nothing:
+    // a buffer's record count bounds the lane's offset and the instruction's
+    // constant, not the scalar offset, which therefore stays 0.  Each group of
+    // kUnroll vectors has a buffer of its own instead, from the group's first
+    // byte (16 * 64 * kUnroll per group) to the row's end, empty where the
+    // group starts past it.
     const int voff = qw * 16;
     auto load = [&](const u32x4 *rv, int u) {
+        const int skip = u / kUnroll * (kUnroll * 64);  // vectors
+        const int left = nq > skip ? (nq - skip) * 16 : 0;
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<u32x4 *>(rv), 0, p.V * 2, 0x00027000);
-        return __builtin_bit_cast(u32x4,
-                                  __builtin_amdgcn_raw_buffer_load_b128(rs, voff, u * 1024, 2));
+            const_cast<u32x4 *>(rv + skip), 0, left, 0x00027000);
+        return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                             rs, voff + u % kUnroll * 1024, 0, 2));
     };
     const bool tail = (wave + 1) * kVecs * 64 > nq;  // some vectors lie past the row's end
 #pragma unroll
