@@ -46,10 +46,11 @@ enum : int32_t {
 // four registers per lane).
 constexpr int kListMaxB = 256;
 
-// The draw at T > 0 with whole rows in registers (one 1024-thread work-group
-// per row): 16-byte vectors per lane, at most.
+// The draw at T > 0 with whole rows in registers (a 1024-thread work-group per
+// row and compute unit): 16-byte vectors per lane, at most.
 constexpr int kRowVecs = 20;
-// Up to this many, two of its work-groups fit a compute unit.
+// Rows of up to this many vectors per lane are taken by work-groups of half the
+// size with twice the vectors, two per compute unit.
 constexpr int kRowVecsTwo = 4;
 
 struct Workspace {

@@ -2099,6 +2099,13 @@ __device__ __forceinline__ unsigned long long scaled_target(unsigned long long u
     return __umul64hi(u, Z);
 }
 
+// The same value, but one whose uses the compiler computes anew: what depends
+// on it is not carried over a loop in registers.
+__device__ __forceinline__ int fresh(int x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
 // The sum launch reads each chunk wave by wave: the kUnroll * 64 vectors of
 // wave w in chunk c are contiguous, [c kChunkVecs + 256 w, + 256), vector u of
 // lane l at 64 u + l; one weight sum per (chunk, wave) then covers a
@@ -2877,10 +2884,10 @@ k_sample_sums_stream(StepParams p) {
 }
 
 // Draw at T > 0 with whole rows in registers: one work-group of 16 waves per
-// compute unit takes a drafted row at a time (rows blockIdx.x, + grid, ... of
-// the batch's drafted rows r < dn[b]), holds it in registers (kVecs 16-byte
-// vectors per lane; wave w the vectors [64 kVecs w, 64 kVecs (w + 1))), and
-// finds the maximum, the weight sums and the drawn token from one read of the
+// compute unit (rows of up to 32768 logits: two of 8 waves) takes a drafted row
+// at a time (rows blockIdx.x, + grid, ... of the batch's drafted rows r < dn[b]),
+// holds it in registers (kVecs 16-byte vectors per lane; wave w the vectors
+// [64 kVecs w, 64 kVecs (w + 1))), and finds the maximum, the weight sums and the drawn token from one read of the
 // row.  As a vector's weights are summed, its registers take the same vector
 // of the work-group's next row, so the reads go on under the sums.  The only
 // hand-off between work-groups is the sequence's arrival count: the last of
@@ -2905,13 +2912,17 @@ struct RowShared {
     Shared s;                      // the accept epilogue's (wave 0)
 };
 
-template <int kVecs, bool kCommit>
-__global__ __launch_bounds__(kRowThreads)
-__attribute__((amdgpu_waves_per_eu(kVecs <= kRowVecsTwo ? 8 : 4))) void k_row_draw(StepParams p) {
+template <int kBlock, int kVecs, bool kCommit>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void
+k_row_draw(StepParams p) {
     __shared__ RowShared sh;
+    constexpr int kBlockWaves = kBlock / 64;
     constexpr int G = kVecs / kUnroll;  // entries of 256 vectors per wave
-    constexpr int E = kRowWaves * G;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    constexpr int E = kBlockWaves * G;
+    // blocks of 64 vectors the draw reads at once (two leave the longest rows
+    // without scratch memory)
+    constexpr int kTogether = kVecs > 16 ? 2 : kUnroll;
+    int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     if (wave == 0) {  // prefix sums of the drafted rows
         int32_t dnq[kListMaxB / 64];
 #pragma unroll
@@ -2958,7 +2969,6 @@ __attribute__((amdgpu_waves_per_eu(kVecs <= kRowVecsTwo ? 8 : 4))) void k_row_dr
         return;
     int n_closed = 0;
     const int nq = p.V >> 3;
-    const int qw = wave * (kVecs * 64) + lane;
     int b, r, dnb;
     locate(j, b, r, dnb);
     auto row_vecs = [&](int bb, int rr) {
@@ -2975,8 +2985,7 @@ __attribute__((amdgpu_waves_per_eu(kVecs <= kRowVecsTwo ? 8 : 4))) void k_row_dr
     // kUnroll vectors has a buffer of its own instead, from the group's first
     // byte (16 * 64 * kUnroll per group) to the row's end, empty where the
     // group starts past it.
-    const int voff = qw * 16;
-    auto load = [&](const u32x4 *rv, int u) {
+    auto load = [&](const u32x4 *rv, int voff, int u) {
         const int skip = u / kUnroll * (kUnroll * 64);  // vectors
         const int left = nq > skip ? (nq - skip) * 16 : 0;
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
@@ -2984,11 +2993,18 @@ __attribute__((amdgpu_waves_per_eu(kVecs <= kRowVecsTwo ? 8 : 4))) void k_row_dr
         return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
                                              rs, voff + u % kUnroll * 1024, 0, 2));
     };
-    const bool tail = (wave + 1) * kVecs * 64 > nq;  // some vectors lie past the row's end
 #pragma unroll
     for (int u = 0; u < kVecs; ++u)
-        A[u] = load(vp, u);
+        A[u] = load(vp, (wave * (kVecs * 64) + lane) * 16, u);
     for (;;) {
+        // (lane numbers, offsets and masks are not carried over the rows in
+        // registers: with them the longest and the shortest rows' kernels used
+        // scratch memory, whose reads waited behind the next row's)
+        tid = fresh(tid);
+        wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        lane = tid & 63;
+        const int qw = wave * (kVecs * 64) + lane;
+        const bool tail = (wave + 1) * kVecs * 64 > nq;  // some vectors lie past the row's end
         // vectors past the row's end become negative NaN, which no maximum
         // takes and whose weight is 0
         if (tail) {
@@ -3012,25 +3028,24 @@ __attribute__((amdgpu_waves_per_eu(kVecs <= kRowVecsTwo ? 8 : 4))) void k_row_dr
             if (lane == 0)
                 sh.mi[wave] = wm;
             __syncthreads();
-            const int k = (int)wave_max_u32(sh.mi[lane & (kRowWaves - 1)]) - 0x8000;
+            const int k = (int)wave_max_u32(sh.mi[lane & (kBlockWaves - 1)]) - 0x8000;
             m = __uint_as_float((uint32_t)k << 16);
             if (k < 0 || k > 0x7F80) {  // no element >= +0, or a positive NaN: as floats
                 float f = __builtin_nanf("");
 #pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    u32x4 c[kUnroll];
+                for (int u = 0; u < kVecs; ++u)
 #pragma unroll
-                    for (int u = 0; u < kUnroll; ++u)
-                        c[u] = A[g * kUnroll + u];
-                    f = fmax_first(f, chunk_max(c));
-                }
+                    for (int w4 = 0; w4 < 4; ++w4) {
+                        f = fmax_first(f, lo_f(A[u][w4]));
+                        f = fmax_first(f, hi_f(A[u][w4]));
+                    }
                 // (a NaN lane has no number; NaN for the row only if every lane is)
                 const bool any = __any(f == f);
                 f = wave_max_f32(f == f ? f : -__builtin_inff());
                 if (lane == 0)
                     sh.mf[wave] = any ? f : __builtin_nanf("");
                 __syncthreads();
-                const float y = sh.mf[lane & (kRowWaves - 1)];
+                const float y = sh.mf[lane & (kBlockWaves - 1)];
                 const bool some = __any(y == y);
                 m = wave_max_f32(y == y ? y : -__builtin_inff());
                 m = some ? m : __builtin_nanf("");
@@ -3050,7 +3065,7 @@ __attribute__((amdgpu_waves_per_eu(kVecs <= kRowVecsTwo ? 8 : 4))) void k_row_dr
             direct = !table_pays(m, p.samp_c);
             if (!direct) {
                 base = table_base(m, p.samp_c);
-                weight_table<kRowThreads>(sh.tab, base, m, p.samp_c);
+                weight_table<kBlock>(sh.tab, base, m, p.samp_c);
             }
             __syncthreads();
         }
@@ -3069,7 +3084,7 @@ __attribute__((amdgpu_waves_per_eu(kVecs <= kRowVecsTwo ? 8 : 4))) void k_row_dr
                     w += x;
                 }
                 if (more)
-                    A[u] = load(vn, u);
+                    A[u] = load(vn, qw * 16, u);
             }
             if (finite) {
                 w = wave_sum_f64(w);
@@ -3080,7 +3095,7 @@ __attribute__((amdgpu_waves_per_eu(kVecs <= kRowVecsTwo ? 8 : 4))) void k_row_dr
         if (!finite) {
             // one-hot at the lowest index of the maximum (0 when all are NaN)
             uint32_t lo = kNoIdx;
-            for (int q = tid; q < nq; q += kRowThreads) {
+            for (int q = tid; q < nq; q += kBlock) {
                 const u32x4 v = vp[q];
                 for (int e = 7; e >= 0; --e) {
                     const uint32_t x = v[e >> 1];
@@ -3115,32 +3130,37 @@ __attribute__((amdgpu_waves_per_eu(kVecs <= kRowVecsTwo ? 8 : 4))) void k_row_dr
                 }
                 // its blocks of 64 vectors, read again together (the next row
                 // fills the registers meanwhile), up to the target's
-                u32x4 v[kUnroll];
                 const int qe = ent * (kUnroll * 64) + lane;
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u) {
-                    const int q = qe + u * 64;
-                    v[u] = vp[q < nq ? q : nq - 1];
-                }
                 unsigned long long w = 0, iv = 0;
-                u32x4 x = v[0];
+                u32x4 x = {0u, 0u, 0u, 0u};
                 int us = -1;
 #pragma unroll
-                for (int u = 0; u < kUnroll; ++u) {
+                for (int u0 = 0; u0 < kUnroll; u0 += kTogether) {
                     if (us < 0) {  // uniform
-                        double d = __builtin_nan("");
-                        if (!direct)
-                            d = vec_lookup(v[u], sh.tab, base);
-                        if (__any(d != d))
-                            d = vec_weight(v[u], m, p.samp_c);
-                        w = qe + u * 64 < nq ? (unsigned long long)d : 0ull;
-                        iv = wave_scan_u64(w);
-                        const unsigned long long tot = readlane_u64(iv, 63);
-                        if (tg < tot || u == kUnroll - 1) {
-                            us = u;
-                            x = v[u];
-                        } else {
-                            tg -= tot;
+                        u32x4 v[kTogether];
+#pragma unroll
+                        for (int i = 0; i < kTogether; ++i) {
+                            const int q = qe + (u0 + i) * 64;
+                            v[i] = vp[q < nq ? q : nq - 1];
+                        }
+#pragma unroll
+                        for (int i = 0; i < kTogether; ++i) {
+                            if (us < 0) {  // uniform
+                                double d = __builtin_nan("");
+                                if (!direct)
+                                    d = vec_lookup(v[i], sh.tab, base);
+                                if (__any(d != d))
+                                    d = vec_weight(v[i], m, p.samp_c);
+                                w = qe + (u0 + i) * 64 < nq ? (unsigned long long)d : 0ull;
+                                iv = wave_scan_u64(w);
+                                const unsigned long long tot = readlane_u64(iv, 63);
+                                if (tg < tot || u0 + i == kUnroll - 1) {
+                                    us = u0 + i;
+                                    x = v[i];
+                                } else {
+                                    tg -= tot;
+                                }
+                            }
                         }
                     }
                 }
@@ -3163,7 +3183,7 @@ __attribute__((amdgpu_waves_per_eu(kVecs <= kRowVecsTwo ? 8 : 4))) void k_row_dr
                 e = e < 0 ? 7 : e;
                 y = (uint32_t)(ent * (kUnroll * 64) + us * 64 + ls) * 8u + (uint32_t)e;
             } else {
-                const uint32_t lo = wave_min_u32(sh.mn[lane & (kRowWaves - 1)]);
+                const uint32_t lo = wave_min_u32(sh.mn[lane & (kBlockWaves - 1)]);
                 y = lo == kNoIdx ? 0u : lo;
             }
             if (lane == 0)
@@ -4033,12 +4053,13 @@ int launch_sample_sums_kernel(const StepParams &p, int64_t grid, hipStream_t str
     return hipGetLastError() == hipSuccess ? SWITCHSD_OK : SWITCHSD_EHIP;
 }
 
-template <int kVecs>
+template <int kBlock, int kVecs>
 static void launch_row_draw_vecs(const StepParams &p, unsigned grid, hipStream_t stream) {
     if (p.commit)
-        hipLaunchKernelGGL((k_row_draw<kVecs, true>), dim3(grid), dim3(kRowThreads), 0, stream, p);
+        hipLaunchKernelGGL((k_row_draw<kBlock, kVecs, true>), dim3(grid), dim3(kBlock), 0, stream,
+                           p);
     else
-        hipLaunchKernelGGL((k_row_draw<kVecs, false>), dim3(grid), dim3(kRowThreads), 0, stream,
+        hipLaunchKernelGGL((k_row_draw<kBlock, kVecs, false>), dim3(grid), dim3(kBlock), 0, stream,
                            p);
 }
 
@@ -4046,15 +4067,15 @@ int launch_row_draw_kernel(const StepParams &p, int64_t grid, hipStream_t stream
     const int vecs = (p.V / 8 + kRowThreads - 1) / kRowThreads;
     const unsigned g = (unsigned)grid;
     if (vecs > 16)
-        launch_row_draw_vecs<20>(p, g, stream);
+        launch_row_draw_vecs<kRowThreads, 20>(p, g, stream);
     else if (vecs > 12)
-        launch_row_draw_vecs<16>(p, g, stream);
+        launch_row_draw_vecs<kRowThreads, 16>(p, g, stream);
     else if (vecs > 8)
-        launch_row_draw_vecs<12>(p, g, stream);
+        launch_row_draw_vecs<kRowThreads, 12>(p, g, stream);
     else if (vecs > kRowVecsTwo)
-        launch_row_draw_vecs<8>(p, g, stream);
+        launch_row_draw_vecs<kRowThreads, 8>(p, g, stream);
     else
-        launch_row_draw_vecs<4>(p, g, stream);
+        launch_row_draw_vecs<kRowThreads / 2, 8>(p, g, stream);
     return hipGetLastError() == hipSuccess ? SWITCHSD_OK : SWITCHSD_EHIP;
 }
 

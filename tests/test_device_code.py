@@ -12,6 +12,14 @@ from paper_2609_20186_amd import build as B
 pytestmark = pytest.mark.skipif(shutil.which(B.HIPCC) is None, reason="no hipcc")
 
 
+class Kernels(dict):
+    """Bodies by name; ``meta``: their descriptors."""
+
+    def __init__(self, bodies, meta):
+        super().__init__(bodies)
+        self.meta = meta
+
+
 @pytest.fixture(scope="module")
 def kernels(tmp_path_factory):
     """Assembly of every kernel of the product library, by (mangled) name."""
@@ -22,8 +30,9 @@ def kernels(tmp_path_factory):
                    check=True, capture_output=True, text=True, timeout=600)
     text = open(out).read()
     bodies = dict(re.findall(r"^(\w+):\s*; @\1\n(.*?)^\.Lfunc_end", text, re.M | re.S))
-    names = re.findall(r"^\s*\.amdhsa_kernel (\w+)", text, re.M)
-    return {n: bodies[n] for n in names}
+    meta = dict(re.findall(r"^\s*\.amdhsa_kernel (\w+)\n(.*?)\.end_amdhsa_kernel", text,
+                           re.M | re.S))
+    return Kernels({n: bodies[n] for n in meta}, meta)
 
 
 def test_buffer_reads_are_bounded(kernels):
@@ -36,3 +45,29 @@ def test_buffer_reads_are_bounded(kernels):
     assert rows and all(loads[n] for n in rows)
     assert sum(map(len, loads.values())) == sum(t.count("buffer_load_") for t in kernels.values())
     assert {n: sorted(set(o)) for n, o in loads.items() if set(o) - {"0"}} == {}
+
+
+def test_row_draw_uses_no_scratch(kernels):
+    """Scratch reads in the row loop would wait behind the next row's loads."""
+    used = {n: int(re.search(r"private_segment_fixed_size (\d+)", kernels.meta[n]).group(1))
+            for n in kernels if "k_row_draw" in n}
+    assert len(used) == 10 and set(used.values()) == {0}, used
+
+
+def test_no_select_reads_a_wide_carry(kernels):
+    """A condition kept in the scalar condition bit must not be overwritten
+    before it is used: no select or branch takes the carry of the upper half of
+    a 64-bit sum or difference (a loop over the draw's blocks was once compiled
+    like that, ran past its end and read out of bounds)."""
+    bad = []
+    for n, t in kernels.items():
+        last = ""
+        for line in t.splitlines():
+            op = line.split()[0] if line.startswith("\ts_") else ""
+            if op.startswith(("s_cselect", "s_cbranch_scc", "s_cmov")):
+                if last.startswith(("s_addc", "s_subb")):
+                    bad.append((n, line.strip()))
+            elif op and not op.startswith(("s_mov", "s_mul_", "s_nop", "s_waitcnt", "s_load",
+                                           "s_cbranch", "s_branch", "s_barrier", "s_ff", "s_flbit")):
+                last = op
+    assert not bad, bad
