@@ -2226,7 +2226,7 @@ __device__ __forceinline__ void store_block_sums(const u32x4 (&A)[kUnroll], int 
 // work-group calls this (the sums are staged in LDS by all of them).
 __device__ void pick_row(const StepParams &p, int b, int r, float m, unsigned long long *keyp,
                          Shared &sh) {
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int tid = fresh(threadIdx.x), wave = tid >> 6, lane = tid & 63;
     const unsigned long long *cs = p.csum + ((int64_t)b * p.R + r) * p.cpr * kWaves;
     const int ncs = p.cpr * kWaves;  // <= 256 (V <= 524288)
     for (int i = tid; i < ncs; i += kThreads)
@@ -2434,7 +2434,7 @@ __device__ void spec_test(const StepParams &p, int b, int r) {
 template <bool kCommit>
 __device__ void row_done(const StepParams &p, int b, int r, int dnb, uint32_t units,
                          uint32_t expected, bool spec, Shared &sh) {
-    const int tid = threadIdx.x;
+    const int tid = fresh(threadIdx.x);
     __builtin_amdgcn_s_waitcnt(0);  // this wave's chunk sums are out
     __syncthreads();
     uint32_t *rt = &p.ws.rtk[(int64_t)b * p.ws.rtk_stride + r];
@@ -2802,7 +2802,9 @@ k_sample_sums_stream(StepParams p) {
         first[q] = carry + inc - cnt;
         carry += __shfl(inc, 63);
     }
-    const int64_t U = carry;
+    // (the sequence, its rows and the chunk range are the same in every lane:
+    // in vector registers they left the closing of a row in scratch memory)
+    const int64_t U = __builtin_amdgcn_readfirstlane(carry);
     const int u0 = (int)(U * blockIdx.x / gridDim.x), u1 = (int)(U * (blockIdx.x + 1) / gridDim.x);
     if (u0 >= u1)
         return;
@@ -2813,8 +2815,8 @@ k_sample_sums_stream(StepParams p) {
         if (m) {
             const int l = 63 - __clzll((long long)m);
             b = 64 * q + l;
-            fb = __shfl(first[q], l);
-            dnb = __shfl(dnq[q], l);
+            fb = __builtin_amdgcn_readlane(first[q], l);
+            dnb = __builtin_amdgcn_readlane(dnq[q], l);
         }
     }
     int r = (u0 - fb) / cpr, c = u0 - fb - r * cpr;
@@ -2841,7 +2843,7 @@ k_sample_sums_stream(StepParams p) {
 #pragma unroll
                     for (int qq = 0; qq < Q; ++qq)
                         if (qq == q)
-                            v = __shfl(dnq[qq], l);
+                            v = __builtin_amdgcn_readlane(dnq[qq], l);
                     ndn = v;
                 }
             }
