@@ -140,6 +140,14 @@ constexpr int kTabHalf = 2560;  // entries per sign
 // (8 x 11 rows of 128256) the table made the launch 12.4 -> 15.2 us, with three
 // (32 x 8 rows) 23.1 -> 20.6 us.
 constexpr int kTableChunks = 3;
+// The same for a row's piece in the streamed sum launch (four work-groups per
+// compute unit instead of six, so less runs beside the making of a table).  All
+// pieces with the table / from 3 / from 5 / from 8 chunks / none, us: 2 x 150
+// rows of 128256 (4.7 chunks a piece) 54.4 / 55.7 / 50.5 / 50.9 / 50.6, 3 x 127
+// (6) 61.0 / - / 56.2 / 60.2 / 60.0, 1 x 250 of 400000 (12) 92.0 / - / 91.4 /
+// 92.9 / 97.1; one-chunk pieces (1 x 101 rows of 128256) 36.7 with, 33.1
+// without.
+constexpr int kTablePieceChunks = 5;
 union SumShared {
     Shared s;
     float tab[2 * kTabHalf];
@@ -2857,8 +2865,9 @@ k_sample_sums_stream(StepParams p) {
         float m = 0.0f;
         const bool active = key_max(key, m);
         unsigned long long *cs = p.csum + ((int64_t)b * p.R + r) * cpr * kWaves;
-        if (done_r == 0) {  // first chunk of this row's piece (the same in every thread)
-            tabled = active && table_pays(m, p.samp_c);
+        if (done_r == 0) {  // first chunk of this row's piece
+            const int piece = cpr - c < u1 - u ? cpr - c : u1 - u;
+            tabled = active && piece >= kTablePieceChunks && table_pays(m, p.samp_c);
             if (tabled) {
                 base = table_base(m, p.samp_c);
                 weight_table<kThreads>(ss.tab, base, m, p.samp_c);
