@@ -428,16 +428,37 @@ int64_t row_slots(int32_t V, int cus) {
     return ((int64_t)V / 8 + 1023) / 1024 <= kRowVecsTwo ? 2 * (int64_t)cus : cus;
 }
 
-// The draw with whole rows in registers, which reads the drafted rows once:
-// one-hot drafts, rows of at most 1024 * 8 * kRowVecs logits, and rows enough
-// for one and a half rounds of its work-groups.  Each takes a row at a time,
-// about 17 us for 128256 logits, after a front launch of 7 us, so with fewer
-// rows a second round would be nearly empty: 256 rows (32 x 8) measured 34 us
-// against 34 us for the maxima and sum launches, 6432 rows (32 x 201, 3344
-// drafted) 239 us against 365 us.
-bool row_draw(int32_t B, int32_t R, int32_t V, const SampleArgs *sa, int cus) {
-    return !sa->qlogits && B <= kListMaxB && V <= 1024 * 8 * kRowVecs &&
-           2 * (int64_t)B * R >= 3 * row_slots(V, cus);
+// The draw with whole rows in registers, which reads the drafted rows once, or
+// the row maxima launch and the sum launch: one-hot drafts, rows of at most
+// 1024 * 8 * kRowVecs logits, rows enough for one and a half rounds of the row
+// draw's work-groups (256 rows of 128256 logits, one round, measured 34 us
+// either way), and the lower of two estimates.  A round of the row draw takes
+// the same time for every row length that a kernel serves, since a row's chain
+// (reads, maximum, table, sums, draw) bounds it: 9.9 us for 512 rows of up to
+// 32768 logits, 9.2, 11.0, 14.2 and 17.5 us for 256 rows in 8, 12, 16 and 20
+// vectors per lane.  The two launches take 7.75 ns a row and 2.5 ns for each
+// 16 KB of it and for each chunk of 16 KB that it touches, and longer before
+// their first row: 2 us in the fused step, whose maxima run beside the front,
+// 6.5 us otherwise, 16 us for the streamed launches of long drafts (trees,
+// several candidates), of whose rows about half are drafted.
+// Measured, row draw / two launches, us: 64 x 64 rows of 12000 logits 86 / 66,
+// 16000 84 / 75, 24000 87 / 93, 32000 88 / 115, 36000 148 / 124, 48000 150 /
+// 149, 65536 156 / 190, 98304 197 / 274; 32 x 64 of 163840 144 / 234; 96 x 13 of
+// 8000 29 / 23; 48 x 8 of 50000 25 / 30, of 128256 40 / 52; in the fused step 96 x
+// 13 of 8000 34 / 24, 66 x 8 of 33000 39 / 30, of 128256 59 / 67; 4 x 201 of
+// 32000 with 8 rows drafted each 13 / 22.
+bool row_draw(int32_t B, int32_t R, int32_t V, const SampleArgs *sa, int cus, bool beside_front) {
+    const int64_t all = (int64_t)B * R, slots = row_slots(V, cus);
+    if (sa->qlogits || B > kListMaxB || V > 1024 * 8 * kRowVecs || 2 * all < 3 * slots)
+        return false;
+    const int64_t chunks = chunks_per_row(V), rows = R > 64 ? all / 2 : all;
+    const double round_us = chunks <= kRowVecsTwo ? 9.9 : chunks <= 8 ? 9.2
+                            : chunks <= 12        ? 11.0
+                            : chunks <= 16        ? 14.2
+                                                  : 17.5;
+    const double row_us = 7.75e-3 + 2.5e-3 * ((double)V / (8 * kChunkVecs) + (double)chunks);
+    const double first_us = R > 64 ? 16.0 : beside_front ? 2.0 : 6.5;
+    return (double)((rows + slots - 1) / slots) * round_us < (double)rows * row_us + first_us;
 }
 
 int row_draw_launch(StepParams p, const SampleArgs *sa, int cus, hipStream_t stream) {
@@ -628,7 +649,7 @@ int verify_launch(const uint16_t *logits, int32_t B, int32_t R, int32_t V, const
         int cus = 0;
         if ((rc = cu_count(&cus)))
             return rc;
-        if (row_draw(B, R, V, sa, cus))
+        if (row_draw(B, R, V, sa, cus, false))
             return row_draw_launch(p, sa, cus, stream);
         if ((rc = prepare_draw(p, sa)))
             return rc;
@@ -795,8 +816,8 @@ int switchsd_step(const switchsd_step_args *a, void *workspace, size_t workspace
     int mode = a->mode;
     if (mode == SWITCHSD_MODE_AUTO)  // short drafts that may use every row: one launch
         mode = cn >= R && R <= 64 ? SWITCHSD_MODE_FUSED : SWITCHSD_MODE_SPLIT;
-    if (mode == SWITCHSD_MODE_FUSED && sampled && row_draw(B, R, V, &sa, cus))
-        mode = SWITCHSD_MODE_SPLIT;  // the draw needs no row maxima beforehand
+    if (mode == SWITCHSD_MODE_FUSED && sampled && row_draw(B, R, V, &sa, cus, true))
+        mode = SWITCHSD_MODE_SPLIT;  // front, then the row draw (which SPLIT then takes too)
     if (mode == SWITCHSD_MODE_FUSED) {
         // the accept epilogue polls at most kMaxPollSlots segment results
         const int64_t cap = kMaxPollSlots / R < kMaxSegs ? kMaxPollSlots / R : kMaxSegs;

@@ -8,6 +8,7 @@ from gpu_helpers import (assert_match, gpu_stages, gpu_step, oracle_step, say, t
                          with_temperature)
 from test_loop_gpu import GpuLoop, oracle_loop, widen
 from test_parity_gpu import AUTO, FUSED, custom_case, workspace_left_clean
+from paper_2609_20186_amd.workloads import f32_to_bf16_bits
 
 pytestmark = pytest.mark.gpu
 
@@ -95,3 +96,64 @@ def test_row_draw_commits():
     np.testing.assert_array_equal(gt, tokens)
     np.testing.assert_array_equal(gd, draft_pos)
     np.testing.assert_array_equal(glag, lag)
+
+
+def pooled_logits(rng, B, R, V):
+    """N(0, 1) rows cut from one pool at random places (fast for many rows)."""
+    pool = f32_to_bf16_bits(np.clip(rng.standard_normal(V + (1 << 20)), -7.5, 7.5)
+                            .astype(np.float32))
+    out = np.empty((B, R, V), np.uint16)
+    for row in out.reshape(B * R, V):
+        at = int(rng.integers(0, 1 << 20))
+        row[:] = pool[at:at + V]
+    return out
+
+
+def verify_sampled(d, dn, T):
+    """switchsd_verify_sample over given drafts; the outputs, and whether the
+    rows were drawn without the weight sums (their space stays as it was: only
+    the maxima and sum launches write it)."""
+    import torch
+    from paper_2609_20186_amd import binding as sd
+    B, R, V = d["logits"].shape
+    dev = to_device(d)
+    o = sd.alloc_outputs(B, R, d["cfg"]["k"])
+    ws = sd.alloc_workspace(B, R, 1, 1)
+    sws = sd.alloc_sample_workspace(B, R, V).fill_(0x5A)
+    sd.switchsd_verify_sample(dev["logits"], T, dev["uniforms"], dev["ntok"], dev["npar"],
+                              torch.from_numpy(dn).cuda(), o["accept_len"], o["accept_node"],
+                              o["bonus"], o["out_tokens"], o["amax"], ws, sws)
+    torch.cuda.synchronize()
+    assert int(ws.count_nonzero()) == 0, "workspace not left zeroed"
+    return o, bool((sws == 0x5A).all())
+
+
+# where the row draw is the slower of the two: short rows (its kernels take a
+# row's chain of steps, however short the row), rows that fill half a kernel's
+# registers, too few rows
+PATHS = {
+    "tiny_rows": (130, 6, 8, False), "short_rows": (96, 13, 8000, False),
+    "many_short_rows": (64, 64, 12000, False), "half_filled": (64, 20, 33000, False),
+    "few_rows": (8, 8, 128256, False), "past_20_vectors": (48, 8, 163848, False),
+    "3_chunks": (96, 13, 20000, True), "4_vectors": (96, 8, 32768, True),
+    "7_chunks": (64, 8, 50000, True), "16_vectors": (48, 8, 128256, True),
+    "long_drafts": (4, 201, 32000, True),
+}
+
+
+@pytest.mark.parametrize("case", sorted(PATHS))
+def test_which_draw_is_taken(case):
+    say(f"[row-draw] path {case}")
+    import torch
+    B, R, V, row = PATHS[case]
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the sizes are those of 256 compute units")
+    rng = np.random.default_rng(240)
+    d = dict(logits=pooled_logits(rng, B, R, V), ntok=rng.integers(0, 6, (B, R)).astype(np.int32),
+             npar=None, cfg=dict(k=R - 1), nn=np.full(B, R, np.int32), T=0.7, bias=0.0,
+             uniforms=rng.integers(0, 2 ** 64, (B, R), dtype=np.uint64),
+             tokens=np.zeros((B, 1), np.int32), lengths=np.ones(B, np.int32),
+             hidden=np.zeros((B, 8), np.uint16), w=np.zeros(8, np.float32))
+    dn = np.full(B, min(R, 8) if R > 64 else R, np.int32)
+    _, by_rows = verify_sampled(d, dn, 0.7)
+    assert by_rows == row
