@@ -21,8 +21,9 @@ def _gpu():
     from paper_2609_20186_amd import binding  # noqa: F401
 
 
-# 1024 * 8 logits per vector and lane: kernels of 4, 8, 12, 16 and 20 vectors
-# (two work-groups per unit with 4, hence more rows)
+# Rows at the edges of the row draw's kernels (8192 logits for each vector of a
+# 1024-thread work-group); the shortest rows, and those just past 32768, are
+# drawn from the weight sums (test_which_draw_is_taken)
 ROWS = {
     "v8": dict(seed=200, B=130, R=6, k=5, V=8, ties=True),
     "4_vectors": dict(seed=201, B=128, R=6, k=5, V=32768),
@@ -98,15 +99,51 @@ def test_row_draw_commits():
     np.testing.assert_array_equal(glag, lag)
 
 
-def pooled_logits(rng, B, R, V):
-    """N(0, 1) rows cut from one pool at random places (fast for many rows)."""
+def pooled_logits(rng, B, R, V, specials=False):
+    """N(0, 1) rows cut from one pool at random places (fast for many rows).
+    ``specials``: some rows negative throughout, all -inf, all NaN, with +inf or
+    with NaN of either sign and zeros among ordinary values."""
     pool = f32_to_bf16_bits(np.clip(rng.standard_normal(V + (1 << 20)), -7.5, 7.5)
                             .astype(np.float32))
     out = np.empty((B, R, V), np.uint16)
     for row in out.reshape(B * R, V):
         at = int(rng.integers(0, 1 << 20))
         row[:] = pool[at:at + V]
+        kind = int(rng.integers(0, 20)) if specials else 20
+        if kind < 3:
+            row |= np.uint16(0x8000)
+        elif kind < 6:
+            row[:] = (0xFF80, 0xFFC0, 0x7FC0)[kind - 3]
+        elif kind == 6:
+            row[rng.integers(0, V, 3)] = 0x7F80
+        elif kind == 7:
+            row[rng.integers(0, V, V // 8)] = rng.choice(
+                np.array([0x7FC1, 0xFFC0, 0x0000, 0x8000, 0xFF80], np.uint16), V // 8)
     return out
+
+
+def many_rows(rng, B, R, V, T, specials=False, tree=False):
+    """Neural drafts of R rows for every sequence, part of each accepted."""
+    npar = None
+    if tree:
+        npar = np.array([[-1] + [int(rng.integers(0, i)) for i in range(1, R)]
+                         for _ in range(B)], np.int32)
+    d = dict(logits=pooled_logits(rng, B, R, V, specials),
+             ntok=rng.integers(0, min(V, 9), (B, R)).astype(np.int32), npar=npar,
+             cfg=dict(lens=(2, 1), kappa=1, k=min(R - 1, 20), theta=1e9),
+             nn=np.full(B, R, np.int32), T=T, bias=0.0,
+             uniforms=rng.integers(0, 2 ** 64, (B, R), dtype=np.uint64),
+             tokens=rng.integers(0, V, (B, 40)).astype(np.int32), lengths=np.full(B, 40, np.int32),
+             hidden=np.zeros((B, 8), np.uint16), w=np.zeros(8, np.float32))
+    # the drawn tokens do not depend on the draft: propose them as children
+    # along part of each draft
+    drawn = oracle_step(d)["amax"]
+    par = np.arange(-1, R - 1)[None].repeat(B, 0) if npar is None else npar
+    at = rng.random((B, R)) < 0.6
+    at[:, 0] = False
+    bi = np.arange(B)[:, None]
+    d["ntok"] = np.where(at, drawn[bi, np.maximum(par, 0)], d["ntok"]).astype(np.int32)
+    return d, oracle_step(d)
 
 
 def verify_sampled(d, dn, T):
@@ -157,3 +194,68 @@ def test_which_draw_is_taken(case):
     dn = np.full(B, min(R, 8) if R > 64 else R, np.int32)
     _, by_rows = verify_sampled(d, dn, 0.7)
     assert by_rows == row
+
+
+# four or more rows for every work-group of each of the row draw's kernels
+# (512 of up to 32768 logits, else 256), ordinary rows between rows without a
+# finite maximum; T = 30 makes no weight table (the table would lack most
+# values).  sums_direct and streamed_sums_direct take the sum launches, whose
+# rows have no table then either.
+ROUNDS = {
+    "512_threads": (128, 16, 16392, 0.7, True, False),
+    "512_threads_long_drafts": (16, 201, 9000, 0.7, True, True),
+    "8_vectors": (64, 16, 49160, 0.7, True, False),
+    "8_vectors_direct": (64, 16, 49160, 30.0, True, False),
+    "12_vectors_tree": (16, 64, 65544, 0.9, True, True),
+    "16_vectors": (64, 16, 98312, 0.7, True, False),
+    "20_vectors": (64, 16, 131080, 0.7, True, False),
+    "20_vectors_direct": (32, 16, 131080, 25.0, True, False),
+    "sums_direct": (64, 20, 33000, 30.0, False, False),
+    "streamed_sums_direct": (2, 201, 163848, 30.0, False, True),
+}
+
+
+@pytest.mark.parametrize("case", sorted(ROUNDS))
+def test_many_rounds(case):
+    say(f"[row-draw] rounds {case}")
+    import torch
+    from paper_2609_20186_amd import binding as sd
+    B, R, V, T, row, tree = ROUNDS[case]
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    d, exp = many_rows(np.random.default_rng(250), B, R, V, T, specials=True, tree=tree)
+    assert (exp["dn"] == R).all() and exp["accept_len"].mean() > 0.3
+    sws = sd.alloc_sample_workspace(B, R, V).fill_(0x5A)
+    got, ws = gpu_step(to_device(d), d, AUTO, sws=sws)
+    assert_match(got, exp, what=case)
+    assert workspace_left_clean(ws, d)
+    o, by_rows = verify_sampled(d, exp["dn"], T)
+    for k in ("amax", "accept_len", "accept_node", "bonus", "out_tokens"):
+        np.testing.assert_array_equal(o[k].cpu().numpy(), exp[k], err_msg=k)
+    if cus == 256:
+        assert by_rows == row and bool((sws == 0x5A).all()) == row
+
+
+def test_row_draw_commits_long_drafts():
+    """Decode steps with the commit, drafts of ten copy candidates: several rows
+    a work-group, the sequences closed after its last."""
+    say("[row-draw] commit, long drafts")
+    d = with_temperature(custom_case(seed=260, B=24, Lmax=600, V=8200, R=201, k=20,
+                                     lens=(3, 2, 1), kappa=1, theta=-0.3, vocab=9, n_cand=10,
+                                     plant=True, ragged=False), 0.6, seed=261)
+    d["nn"][:] = 201
+    d = widen(d, 80)
+    outs, tokens, lengths, draft_pos, lag = oracle_loop(d, 3)
+    assert outs[0]["dn"].sum() > 4 * 512 and 0 < outs[0]["use_copy"].sum() < 24
+    g = GpuLoop(d, AUTO)
+    g.sws.fill_(0x5A)
+    for s in range(3):
+        g.step()
+        assert_match({k: v.cpu().numpy() for k, v in g.out.items()}, outs[s], what=f"step {s}")
+    import torch
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert bool((g.sws == 0x5A).all())
+    gt, gl, gd, glag = g.state()
+    np.testing.assert_array_equal(gl, lengths)
+    np.testing.assert_array_equal(gt, tokens)
+    np.testing.assert_array_equal(gd, draft_pos)
+    np.testing.assert_array_equal(glag, lag)
