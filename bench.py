@@ -30,15 +30,6 @@ sys.path.insert(0, ROOT)
 from paper_2609_20186_amd import workloads as W  # noqa: E402
 
 HBM_PEAK_GBPS = 8000.0
-# VALU issue rate: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz (a wave64 op takes 4
-# cycles on one SIMD) = 39.3 T lane-ops/s; one FMA is one op here
-VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
-# VALU ops per logit of the draw at T > 0: about 1.5 in the row-maximum pass
-# and 19.3 in the sum pass (the compiled chunk loop of k_sample_sums issues 617
-# VALU instructions per 32 logits of a lane: unpack, subtract, scale, clamp,
-# rint, reduce, 6 fused multiply-adds, convert, ldexp, floor, widen to
-# binary64, accumulate, and the wave sums)
-SAMPLE_OPS_PER_LOGIT = 20.8
 METRIC = "speculation-control steps/s + verify-argmax HBM GB/s (% peak), B=32 V=128256"
 PROFILES = os.path.join(ROOT, "profiles")
 ROTATE_BYTES = 512 << 20
@@ -65,12 +56,45 @@ def algorithmic_bytes(wl, rows_read, d_sel=None):
     return ins + logits + outs, logits
 
 
-def resolve_mode(wl, mode):
-    """The launch the library's AUTO mode picks (switchsd_step)."""
+def resolve_mode(wl, mode, by_rows=False):
+    """The launch the library's AUTO mode picks (switchsd_step); ``by_rows``: the
+    draw at T > 0 holds whole rows in registers, which takes a fused step apart
+    into the front launch and the row draw."""
+    if by_rows:
+        return 2
     if mode:
         return mode
     cn = 1 + max(1, wl.n_cand) * wl.k
     return 1 if cn >= wl.R and wl.R <= 64 else 2
+
+
+def drawn_by_rows(torch, sws, run):
+    """Whether ``run`` drew whole rows from registers: then it writes no weight
+    sums, and the sample workspace stays as it was."""
+    sws.fill_(0x5A)
+    run()
+    torch.cuda.synchronize()
+    return bool((sws == 0x5A).all())
+
+
+def sampled_launches(by_rows, q, q_merged):
+    """The kernels of a verification at T > 0, in order."""
+    if by_rows:
+        return ["row draw from one read"]
+    if not q:
+        return ["row maxima", "weight sums with the draw"]
+    return (["row maxima of p and q"] if q_merged else ["row maxima", "q row maxima"]) + \
+        ["weight sums with the accept tests", "residual draw"]
+
+
+def launch_names(mode, T, by_rows, q, q_merged):
+    """The kernels of one step."""
+    if T <= 0:
+        return {1: "fused, 1 kernel", 2: "split, 2 kernels"}[mode]
+    ks = sampled_launches(by_rows, q, q_merged)
+    if mode == 1:
+        return f"fused, {len(ks)} kernels: front with " + ", ".join(ks)
+    return f"split, {1 + len(ks)} kernels: front, " + ", ".join(ks)
 
 
 def upload(d):
@@ -414,11 +438,11 @@ def main():
     sel = plant_with_library(wl, d, sd)
 
     base = upload(d)
-    # bytes one step reads (the drafted rows for a split step, every row the
-    # fused launch reads otherwise): enough copies that > 512 MB lie between
-    # two uses of one copy
+    # bytes one step reads (the drafted rows for a split step or at T > 0, every
+    # row the fused launch reads otherwise): enough copies that > 512 MB lie
+    # between two uses of one copy
     cn = 1 + max(1, wl.n_cand) * wl.k
-    if resolve_mode(wl, args.mode) == sd.MODE_FUSED:
+    if resolve_mode(wl, args.mode) == sd.MODE_FUSED and args.temperature == 0:
         rows0 = np.maximum(np.clip(d["nn"], 1, wl.R), cn) if cn < wl.R else np.full(wl.B, wl.R)
     else:
         rows0 = sel["dn"]
@@ -471,8 +495,8 @@ def main():
         for k, v in o.items():
             assert torch.equal(v.cpu(), o0[k]), f"rotation set disagrees on {k}"
 
-    mode = resolve_mode(wl, args.mode)
-    cn = 1 + max(1, wl.n_cand) * wl.k
+    step_by_rows = T > 0 and drawn_by_rows(torch, sws, lambda: run(0, 1))
+    mode = resolve_mode(wl, args.mode, step_by_rows)
     if mode == sd.MODE_FUSED:
         rows_read = np.maximum(np.clip(d["nn"], 1, wl.R), cn) if cn < wl.R \
             else np.full(wl.B, wl.R)
@@ -508,6 +532,7 @@ def main():
 
     nv = max(200, args.steps // 4)
     run_verify(0, 20)
+    verify_by_rows = T > 0 and drawn_by_rows(torch, sws, lambda: run_verify(0, 1))
     v_per = event_timings(torch, stream, run_verify, nv, max(1, args.repeats))
     vms = float(np.median(v_per))
     vbytes = int(np.sum(sel["dn"])) * wl.V * 2
@@ -549,7 +574,7 @@ def main():
 
     # the dominant kernel: the fused launch, or the verify launch of a split
     # step; at T > 0 the verification's launches together.  `achieved` divides
-    # the algorithmic bytes (ops) of one launch (call) by its own duration,
+    # the algorithmic bytes of one launch (call) by its own duration,
     # each launch bracketed by its own HIP events on the launch stream
     launch_ms = ms
     # the row maxima launch also takes the q rows unless it streams long
@@ -559,19 +584,15 @@ def main():
     q_merged = (qdev is not None and max(1, wl.n_cand) == 1 and
                 not (mode == sd.MODE_SPLIT and listed))
     if T > 0:
+        # each drafted row counted once (with q the draft's rows too), however
+        # often the launches read it
         qrows = 0 if qdev is None else int(np.sum(np.clip(sel["dn"] - 1, 0, None) *
                                                   (sel["use_copy"] == 0)))
-        ops = (vbytes / 2 + qrows * wl.V) * SAMPLE_OPS_PER_LOGIT
-        dom = {"kernel": ("sampled verification (row maxima of p and q, then weight sums with "
-                          "the accept tests, then the residual draw: 3 launches)"
-                          if q_merged_verify else
-                          "sampled verification (row maxima, q row maxima, weight sums with the "
-                          "accept tests, residual draw: 4 launches)"
-                          if qdev is not None else
-                          "sampled verification (row maxima, then weight sums with the draw: "
-                          "2 launches)"),
-               "bound": "alu", "unit": "TOP/s (VALU lane-ops)", "peak": round(VALU_PEAK_TOPS, 1),
-               "gbps": ops / (vms * 1e-3) / 1e12, "bytes": int(ops), "ms": vms,
+        sbytes = vbytes + qrows * wl.V * 2
+        kernels = sampled_launches(verify_by_rows, qdev is not None, q_merged_verify)
+        dom = {"kernel": f"sampled verification ({', '.join(kernels)}: {len(kernels)} "
+                         f"launch{'es' if len(kernels) > 1 else ''})",
+               "gbps": sbytes / (vms * 1e-3) / 1e9, "bytes": sbytes, "ms": vms,
                "traffic_file": f"traffic_sampled_verify_{wl.name}.json"}
     elif mode == sd.MODE_FUSED:
         dom = {"kernel": "k_switchsd (fused step)", "gbps": alg / (launch_ms * 1e-3) / 1e9,
@@ -610,20 +631,12 @@ def main():
                                f" W={max(1, wl.n_cand)} ngram={list(wl.ngram_lens)}"
                                f" kappa={wl.kappa}" + (f" T={T}" if T > 0 else ""),
                    "global_batch": wl.B, "seq_len": wl.L, "parallelism": "none (1 GPU)",
-                   "launch": {1: "fused, 1 kernel", 2: "split, 2 kernels"}[mode] +
-                             ("" if T <= 0 else
-                              " + 1 kernel for the weight sums and the draw at T > 0"
-                              if qdev is None else
-                              (" (with the q row maxima)" if q_merged else
-                               " + 1 kernel for the q row maxima") +
-                              " + 2 kernels for the weight sums with the accept tests and the"
-                              " residual draw"),
+                   "launch": launch_names(mode, T, step_by_rows, qdev is not None, q_merged),
                    "rotation_sets": nrot},
-        "roofline": {"bound": dom.get("bound", "hbm"), "achieved": round(dom["gbps"], 1),
-                     "peak": dom.get("peak", HBM_PEAK_GBPS), "unit": dom.get("unit", "GB/s"),
-                     "frac": round(dom["gbps"] / dom.get("peak", HBM_PEAK_GBPS), 4),
+        "roofline": {"bound": "hbm", "achieved": round(dom["gbps"], 1), "peak": HBM_PEAK_GBPS,
+                     "unit": "GB/s", "frac": round(dom["gbps"] / HBM_PEAK_GBPS, 4),
                      "traffic": traffic, "kernel": dom["kernel"],
-                     ("algorithmic_ops_per_call" if T > 0 else "algorithmic_bytes_per_launch"):
+                     ("algorithmic_bytes_per_call" if T > 0 else "algorithmic_bytes_per_launch"):
                          dom["bytes"]},
         "timing": {"repeats": len(per_step), "steps_per_repeat": args.steps,
                    "ms_per_step_median": round(ms, 5),

@@ -27,6 +27,19 @@ def test_auto_mode_matches_the_library_rule():
     assert bench.resolve_mode(W.WORKLOADS["C5"], 0) == 2
     assert bench.resolve_mode(W.WORKLOADS["C2W10"], 0) == 2
     assert bench.resolve_mode(W.WORKLOADS["C5"], 1) == 1   # an explicit mode is kept
+    # a draw from whole rows needs no row maxima: the step is split
+    assert bench.resolve_mode(W.WORKLOADS["C2"], 0, by_rows=True) == 2
+    assert bench.resolve_mode(W.WORKLOADS["C2"], 1, by_rows=True) == 2
+
+
+def test_launches_of_a_sampled_verification():
+    assert len(bench.sampled_launches(True, False, False)) == 1
+    assert len(bench.sampled_launches(False, False, False)) == 2
+    assert len(bench.sampled_launches(False, True, True)) == 3
+    assert len(bench.sampled_launches(False, True, False)) == 4
+    assert bench.launch_names(2, 0.7, True, False, False).startswith("split, 2 kernels: front, row")
+    assert bench.launch_names(1, 0.7, False, False, False).startswith("fused, 2 kernels: front with")
+    assert bench.launch_names(1, 0.0, False, False, False) == "fused, 1 kernel"
 
 
 def test_c2_algorithmic_bytes():
