@@ -210,10 +210,14 @@ int switchsd_verify_accept(const uint16_t *logits, int32_t B, int32_t R, int32_t
  *   V % 8 == 0 and V <= 524288; sample_workspace of
  *   switchsd_sample_workspace_bytes(B, R, V) bytes, 256-byte aligned, no
  *   initialization needed; other arguments as in switchsd_verify_accept.
- *   Launches: the row maxima, then the weight sums, in which one work-group per
- *   row draws the row's token (without q, R <= 64 and B * R no larger than the
- *   compute-unit count: the row's first, polling the others' sums; else the
- *   last to arrive); with q the first launch also takes the q row maxima (a
+ *   Launches: without q, B <= 256, V <= 163840 and B * R at least one and a half
+ *   times what fits the device at once (a row per compute unit, two of up to
+ *   32768 logits), where row count and length make it the faster form, one
+ *   launch that holds whole rows in registers and needs neither row maxima nor
+ *   the sample workspace.  Else the row maxima, then the weight sums, in which
+ *   one work-group per row draws the row's token (without q, R <= 64 and B * R
+ *   no larger than the compute-unit count: the row's first, polling the others'
+ *   sums; else the last to arrive); with q the first launch also takes the q row maxima (a
  *   launch of their own for streamed long drafts), the weight sums take the
  *   accept tests, and the residual draw comes last. */
 int switchsd_verify_sample(const uint16_t *logits, int32_t B, int32_t R, int32_t V,
@@ -250,6 +254,10 @@ typedef enum {
     SWITCHSD_MODE_FUSED = 1, /* one launch; reads rows r < max(nn[b], 1 + W k)                */
     SWITCHSD_MODE_SPLIT = 2  /* two launches; reads only rows r < dn[b] of the chosen draft  */
 } switchsd_mode;
+/* At T > 0 the draw adds a launch (with draft_logits two or three), except
+ * where it holds whole rows in registers (see switchsd_verify_sample): the step
+ * is then the front launch and that draw, which reads rows r < dn[b] once, in
+ * every mode (FUSED too, also when AUTO chose it). */
 
 /* All arguments of one step (steps 1-4 in order).  Inputs as in the stage
  * calls above; every output pointer is required except amax. */

@@ -2133,8 +2133,11 @@ __device__ __forceinline__ void load_chunk_w(u32x4 (&v)[kUnroll], const u32x4 *v
 // weight once per work-group and row, into LDS, and look it up per logit: 6.4
 // VALU operations and one 4-byte LDS read (about 6.5 cycles per wave and
 // compute unit at random entries) instead of the 17 operations of samp_weight,
-// which bounded the launches.  The values are samp_weight's own, so the sums
-// are the same integers.  Measured per launch at T = 0.7: 32 x 8 rows of 128256
+// which bounded the launches.  With the table itself (20 weights a lane, for 96
+// logits in the 32 x 8 launch below), the direct vectors, the clamped addresses,
+// the copies of the next chunk and the draw, the launch issues 16.8 VALU
+// instructions a logit (20.4 without tables), the row draw 10.9 with its
+// maximum.  The values are samp_weight's own, so the sums are the same integers.  Measured per launch at T = 0.7: 32 x 8 rows of 128256
 // 23.1 -> 20.6 us, the same with q 34.8 -> 29.5 us, 3344 rows streamed 241 ->
 // 205 us.  One table per 1024-thread work-group instead (four chunks at once)
 // took 25.0 us for the 32 x 8 rows.
@@ -2147,9 +2150,10 @@ __device__ __forceinline__ void load_chunk_w(u32x4 (&v)[kUnroll], const u32x4 *v
 //
 // The table pays where few logits are that small: bottom = 2^-20 of the
 // power of two above |m| + 41 / c; with |m| at 4.5 standard deviations and
-// |m| + 41 / c = 128 |m|, 45% of the 512-logit vectors of a wave would hold one
-// and cost about what the direct form does, so beyond that ratio the row is
-// computed directly.
+// |m| + 41 / c = 128 |m|, a third of the 512-logit vectors of a wave would hold
+// one, and with the table made the row costs about what the direct form does,
+// so beyond that ratio it is computed directly.  (At T = 0.7 and N(0, 1) logits
+// the bottom is 2^-15 and 1.2% of the vectors hold one.)
 __device__ __forceinline__ float table_limit(float m, float c) {
     return __builtin_fabsf(m) + 41.0f / c;
 }
@@ -2903,12 +2907,12 @@ k_sample_sums_stream(StepParams p) {
 // of the work-group's next row, so the reads go on under the sums.  The only
 // hand-off between work-groups is the sequence's arrival count: the last of
 // its rows runs the accept epilogue.  Nothing waits for another work-group.
-// Bound by a row's chain: its reads (about 12 us of 17 for 128256 logits with
+// Bound by a row's chain: its reads (about 12 us of 16 for 128256 logits with
 // every compute unit reading), the table before the sums and the draw after
-// them, under which only the next row's reads go on.  3344 drafted rows at
-// T = 0.7: 206-226 us, against 133 us for the maxima and 205 us for the sums
-// in two streamed launches; a step with ten candidates per sequence (32) 368 ->
-// 219 us.
+// them, under which only the next row's reads go on (4.2 TB/s of the 6.5 that
+// a longer read reaches).  Verification of 3344 drafted rows at T = 0.7, 32 x
+// 201: 208 us, against 373 us for the two streamed launches without tables; a
+// step with those drafts 222 us against 376 us.
 constexpr int kRowThreads = 1024;
 constexpr int kRowWaves = kRowThreads / 64;
 constexpr int kRowMaxVecs = kRowVecs;  // per lane: V <= 1024 * 8 * kRowMaxVecs
